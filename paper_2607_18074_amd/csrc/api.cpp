@@ -34,6 +34,7 @@
 #include "../../include/sobek.h"
 #include "jit.h"
 #include "plan.h"
+#include "split.h"
 #include "tables.h"
 
 using sobek::Plan;
@@ -586,9 +587,75 @@ bool keeps_all(const Plan& p, uint64_t mask) {
   return mask && G <= 64 && mask == (G == 64 ? ~(uint64_t)0 : (((uint64_t)1 << G) - 1));
 }
 
+// Weight-gradient split partials of group gi: a region of nsplit_for(p, g, ncap d_g) * D_g * C_g
+// floats per group, the groups' regions in group order (ncap = the pass's receiver capacity).
+float* ga_partials(const Plan& p, const WsPlan& w, void* ws, int gi) {
+  float* P = (float*)((char*)ws + w.off_P);
+  for (int h = 0; h < gi; ++h) {
+    const sobek::Group& g = p.groups[h];
+    P += (size_t)nsplit_for(p, g, (int64_t)w.ncap * g.d) * g.D * g.C;
+  }
+  return P;
+}
+
+// The split products (device/split.hip) of output groups [glo, ghi) for receivers [r0, r0 + n) in one
+// launch; S holds group blocks s_ncap receivers apart (0: one group, at S).
+//
+// out (+)= S A.  Few row tiles share out the reduction: about kSaTarget blocks, at least 128 k each,
+// within the pass's partial region; the kernel derives each group's split from ns.
+int split_mix(const Plan& p, int glo, int ghi, int r0, int n, const WsPlan& w, void* ws, const float* S,
+              int64_t s_ncap, const float* W, float* out, int acc, hipStream_t s) {
+  auto shape = [&](int ns, int64_t& blocks, size_t& floats) {
+    blocks = 0;
+    floats = 0;
+    for (int i = glo; i < ghi; ++i) {
+      const sobek::Group& g = p.groups[i];
+      const int64_t nz = cdiv(g.D, std::max<int64_t>(128, cdiv(cdiv(g.D, ns), 32) * 32));
+      blocks += (int64_t)cdiv((int64_t)n * g.d, 128) * cdiv(g.C, sobek::split_bn(g.C)) * nz;
+      floats += (size_t)nz * n * g.d * g.C;
+    }
+  };
+  int64_t base, blocks;
+  size_t floats;
+  shape(1, base, floats);
+  int ns = 1;
+  if (n > 0 && base * 2 <= kSaTarget) ns = (int)std::min<int64_t>(kSaMaxSplit, (kSaTarget + base - 1) / base);
+  for (shape(ns, blocks, floats); ns > 1 && floats > w.kfloats; shape(--ns, blocks, floats)) {}
+  float* K = ns > 1 ? (float*)((char*)ws + w.off_K) : nullptr;
+  long long cap = s_ncap;
+  LAUNCH(p.k.sp3_sa, (unsigned)blocks, 1, 1, s, S, cap, r0, n, W, (const int*)p.d_ktab, out, acc, K, ns, glo, ghi);
+  if (ns > 1) {
+    int64_t quads = 0;
+    for (int i = glo; i < ghi; ++i) quads += (int64_t)n * p.groups[i].d * p.groups[i].C / 4;
+    LAUNCH(p.k.sp3_red, cdiv(quads, 256), 1, 1, s, (const float*)K, r0, n, out, acc, ns, glo, ghi);
+  }
+  return SOBEK_OK;
+}
+
+// gW = S^T mbar over calls: split partials of every group (regions as ga_partials), summed on the last
+int split_ga(const Plan& p, int glo, int ghi, int r0, int n, const WsPlan& w, void* ws, const float* S,
+             int64_t s_ncap, const float* M, float* gW, bool first_chunk, bool last_chunk, hipStream_t s) {
+  float* P = ga_partials(p, w, ws, glo);
+  int64_t blocks = 0, quads = 0;
+  for (int i = glo; i < ghi; ++i) {
+    const sobek::Group& g = p.groups[i];
+    blocks += (int64_t)cdiv(g.D, 128) * cdiv(g.C, sobek::split_bn(g.C)) * nsplit_for(p, g, (int64_t)w.ncap * g.d);
+    quads += g.D * g.C / 4;
+  }
+  long long cap = w.ncap, sn = s_ncap;
+  int acc = first_chunk ? 0 : 1;
+  LAUNCH(p.k.sp3_ga, (unsigned)blocks, 1, 1, s, S, sn, r0, n, M, P, cap, acc, glo, ghi);
+  if (last_chunk) LAUNCH(p.k.sp3_gared, cdiv(quads, 256), 1, 1, s, (const float*)P, cap, (const int*)p.d_ktab, gW, glo, ghi);
+  return SOBEK_OK;
+}
+
 // out(i, m_o, w) (+)= S_g A_g for group g; Sg holds the group's rows of receivers [r0, r0 + n)
 int mix_group(const Plan& p, const sobek::Group& g, int r0, int n, const WsPlan& w, void* ws, const float* Sg,
               const float* W, float* out, int acc, hipStream_t s) {
+  if (p.split) {
+    const int gi = (int)(&g - p.groups.data());
+    return split_mix(p, gi, gi + 1, r0, n, w, ws, Sg, 0, W, out, acc, s);
+  }
   float* K = (float*)((char*)ws + w.off_K);
   int nrows = n * g.d, D = (int)g.D, dg = g.d, Cg = g.C, off = g.off, CX = p.dim_out;
   if (p.mode == SOBEK_MODE_UVU) {
@@ -616,6 +683,7 @@ int mix_group(const Plan& p, const sobek::Group& g, int r0, int n, const WsPlan&
 // out(i, m_o, w) (+)= S_g A_g for every group
 int run_mix(const Plan& p, const Chunk& c, const WsPlan& w, void* ws, const float* S, const float* W, float* out,
             int acc, hipStream_t s) {
+  if (p.split) return split_mix(p, 0, (int)p.groups.size(), c.r0, c.n, w, ws, S, w.ncap, W, out, acc, s);
   for (auto& g : p.groups)
     if (int rc = mix_group(p, g, c.r0, c.n, w, ws, state_at(p, S, (size_t)w.ncap * g.s_off), W, out, acc, s))
       return rc;
@@ -627,7 +695,22 @@ int run_mix(const Plan& p, const Chunk& c, const WsPlan& w, void* ws, const floa
 // s_ncap receivers apart (the chunk slot, or a state kept for every receiver)
 int run_sbar(const Plan& p, const Chunk& c, int64_t s_ncap, const float* M, const float* W, float* Sbar,
              hipStream_t s) {
+  if (p.split) {
+    // column tiles per block: all of a row block's when that gives about four blocks per CU, else fewer
+    // (at least two, so that a block's mbar planes are used again)
+    int64_t tiles = 0;
+    for (auto& g : p.groups)
+      if (g.C <= 128) tiles += (int64_t)cdiv((int64_t)c.n * g.d, 128) * cdiv(g.D, 64);
+    int tpb = (int)std::max<int64_t>(2, tiles / 1024);
+    int64_t blocks = 0;
+    for (auto& g : p.groups)
+      if (g.C <= 128) blocks += (int64_t)cdiv((int64_t)c.n * g.d, 128) * cdiv(cdiv(g.D, 64), tpb);
+    int r0 = c.r0, n = c.n;
+    long long cap = s_ncap;
+    LAUNCH(p.k.sp3_sbar, (unsigned)blocks, 1, 1, s, M, r0, n, W, (const int*)p.d_ktab, Sbar, cap, tpb);
+  }
   for (auto& g : p.groups) {
+    if (p.split && g.C <= 128) continue;
     float* Sg = Sbar + (size_t)s_ncap * g.s_off;
     int nrows = c.n * g.d, D = (int)g.D, dg = g.d, Cg = g.C, off = g.off, CX = p.dim_out, r0 = c.r0;
     if (p.mode == SOBEK_MODE_UVU)
@@ -649,17 +732,6 @@ int run_sbar(const Plan& p, const Chunk& c, int64_t s_ncap, const float* M, cons
   return SOBEK_OK;
 }
 
-// Weight-gradient split partials of group gi: a region of nsplit_for(p, g, ncap d_g) * D_g * C_g
-// floats per group, the groups' regions in group order (ncap = the pass's receiver capacity).
-float* ga_partials(const Plan& p, const WsPlan& w, void* ws, int gi) {
-  float* P = (float*)((char*)ws + w.off_P);
-  for (int h = 0; h < gi; ++h) {
-    const sobek::Group& g = p.groups[h];
-    P += (size_t)nsplit_for(p, g, (int64_t)w.ncap * g.d) * g.D * g.C;
-  }
-  return P;
-}
-
 // gW += S_g^T mbar_g over the rows of receivers [r0, r0 + n), deterministic: each call adds its
 // rows into fixed split partials (the group's first call overwrites them), and its last call sums
 // the splits in fixed order into W's layout.  The split count follows the pass's receiver
@@ -667,6 +739,7 @@ float* ga_partials(const Plan& p, const WsPlan& w, void* ws, int gi) {
 int ga_group(const Plan& p, int gi, int r0, int n, const WsPlan& w, void* ws, const float* Sg, const float* M,
              float* gW, bool first_chunk, bool last_chunk, hipStream_t s) {
   const sobek::Group& g = p.groups[gi];
+  if (p.split) return split_ga(p, gi, gi + 1, r0, n, w, ws, Sg, 0, M, gW, first_chunk, last_chunk, s);
   float* P = ga_partials(p, w, ws, gi);
   int nrows = n * g.d, D = (int)g.D, dg = g.d, Cg = g.C, off = g.off, CX = p.dim_out;
   int ns = nsplit_for(p, g, (int64_t)w.ncap * g.d);
@@ -701,6 +774,8 @@ int ga_group(const Plan& p, int gi, int r0, int n, const WsPlan& w, void* ws, co
 // block, group blocks s_ncap receivers apart (the chunk slot, or a retained full state).
 int run_ga(const Plan& p, const Chunk& c, const WsPlan& w, void* ws, const float* S, int64_t s_ncap, const float* M,
            float* gW, bool first_chunk, bool last_chunk, hipStream_t s) {
+  if (p.split)
+    return split_ga(p, 0, (int)p.groups.size(), c.r0, c.n, w, ws, S, s_ncap, M, gW, first_chunk, last_chunk, s);
   for (int gi = 0; gi < (int)p.groups.size(); ++gi)
     if (int rc = ga_group(p, gi, c.r0, c.n, w, ws, state_at(p, S, (size_t)s_ncap * p.groups[gi].s_off), M, gW,
                           first_chunk, last_chunk, s))
@@ -917,6 +992,20 @@ int load_receiver_route(Plan& p, hipModule_t m) {
   return SOBEK_OK;
 }
 
+// split channel products, a module of their own
+int load_split(Plan& p) {
+  if (!sobek::split_plan(p)) return SOBEK_OK;
+  int rc;
+  if ((rc = load_module(sobek::generate_split_source(p), p.k.module_sp3))) return rc;
+  hipModule_t m = p.k.module_sp3;
+  if ((rc = get_fn(m, p.k.sp3_sa, "sobek_sp3_sa")) || (rc = get_fn(m, p.k.sp3_red, "sobek_sp3_red")) ||
+      (rc = get_fn(m, p.k.sp3_ga, "sobek_sp3_ga")) || (rc = get_fn(m, p.k.sp3_gared, "sobek_sp3_gared")) ||
+      (rc = get_fn(m, p.k.sp3_sbar, "sobek_sp3_sbar")))
+    return rc;
+  p.split = true;
+  return SOBEK_OK;
+}
+
 // channelwise state-free kernels, with the route choice from their scratch and register use
 int load_uvu(Plan& p, hipModule_t m) {
   int rc;
@@ -1066,6 +1155,7 @@ int sobek_plan_create(const sobek_irrep* in, int n_in, int lmax, const sobek_irr
     if ((rc = load_receiver_route(p, p.k.module))) return rc;
     p.rr_loaded = true;
   }
+  if ((rc = load_split(p))) return rc;
   HIPCHK(hipMalloc(&p.d_ktab, std::max<size_t>(4, p.ktab.size() * 4)));
   HIPCHK(hipMemcpy(p.d_ktab, p.ktab.data(), p.ktab.size() * 4, hipMemcpyHostToDevice));
   auto blocks = [](const std::vector<sobek::Irrep>& v) {
@@ -1096,6 +1186,7 @@ int sobek_jit_compile(const sobek_irrep* in, int n_in, int lmax, const sobek_irr
     // SOBEK_JIT_STATE_FREE_ONLY=1: channelwise plans compile only the part a plan loads at creation
     const char* sf = std::getenv("SOBEK_JIT_STATE_FREE_ONLY");
     if (p.source_u.empty() || !sf || std::strcmp(sf, "1") != 0) sobek::jit_compile(p.source);
+    if (sobek::split_plan(p)) sobek::jit_compile(sobek::generate_split_source(p));
     if (materialized_supported(p)) sobek::jit_compile(sobek::generate_materialized_source(p));
     const char* gs = std::getenv("SOBEK_JIT_GROUPS");
     if (gs && std::strcmp(gs, "1") == 0) sobek::jit_compile(sobek::generate_group_source(p));
@@ -1169,6 +1260,7 @@ int sobek_plan_destroy(sobek_plan plan) {
   if (p.k.module_u) (void)hipModuleUnload(p.k.module_u);
   if (p.k.module_mat) (void)hipModuleUnload(p.k.module_mat);
   if (p.k.module_grp) (void)hipModuleUnload(p.k.module_grp);
+  if (p.k.module_sp3) (void)hipModuleUnload(p.k.module_sp3);
   if (plan->side) (void)hipStreamDestroy(plan->side);
   if (plan->fork) (void)hipEventDestroy(plan->fork);
   if (plan->join) (void)hipEventDestroy(plan->join);

@@ -89,6 +89,8 @@ struct Kernels {
   std::vector<std::array<hipFunction_t, 3>> fwd_grp;  // per group: S, dS_r, dS
   hipModule_t module_mat = nullptr;  // the materialized-forward baseline (compiled on first use)
   hipFunction_t mat_w = nullptr, mat_msg = nullptr, mat_reduce = nullptr;
+  hipModule_t module_sp3 = nullptr;  // split channel products (split_plan)
+  hipFunction_t sp3_sa = nullptr, sp3_red = nullptr, sp3_ga = nullptr, sp3_gared = nullptr, sp3_sbar = nullptr;
   hipModule_t module_u = nullptr;  // channelwise plans: the state-free kernels and the common ones
   hipFunction_t fwd_S = nullptr, fwd_dS = nullptr, fwd_dS_r = nullptr;
   hipFunction_t bwd_E = nullptr, dbwd_E = nullptr, dbwd_E_r = nullptr;
@@ -137,6 +139,7 @@ struct Plan {
   std::vector<int> dead_out;    // output irreps no path writes (their outputs are zero)
   std::string source;           // generated HIP source
   std::string source_u;         // channelwise plans with the state-free kernels: that part alone
+  bool split = false;           // the split channel products apply
   bool rr_loaded = false;       // the receiver-route kernels are loaded
   std::string cache_key;
   Kernels k;

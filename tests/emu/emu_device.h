@@ -32,6 +32,9 @@
 #define __builtin_amdgcn_wave_barrier() emu_wave_sync(__LINE__)
 #define __builtin_amdgcn_rsqf(x) (1.0f / sqrtf(x))
 #define __builtin_amdgcn_readlane(v, l) emu_readlane((v), (l), __LINE__)
+#define __builtin_amdgcn_readfirstlane(v) (v)
+#define __builtin_amdgcn_mov_dpp(v, ctrl, rm, bm, bc) emu_mov_dpp((v), (ctrl), __LINE__)
+#define __builtin_amdgcn_ds_read_tr16_b64_v4i16(p) emu_ds_read_tr16((const void*)(uintptr_t)(p), __LINE__)
 #define __ballot(p) emu_ballot((p), __LINE__)
 #define __shfl_xor(...) emu_shfl_xor_(__LINE__, __VA_ARGS__)
 #define __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, x, y, z) emu_mfma_4x4x1((a), (b), (c), __LINE__)
@@ -76,6 +79,33 @@ static inline T emu_shfl_xor_(int site, T v, int mask, int width = 64) {
   T r;
   memcpy(&r, s + 64 * idx, sizeof(T));
   return r;
+}
+
+// DPP move: quad permutations (0x00 - 0xff), row_ror:n (0x121 - 0x12f: lane l takes lane
+// (l - n) mod 16 of its 16-lane row), row_mirror (0x140), row_half_mirror (0x141)
+static inline int emu_mov_dpp(int v, int ctrl, int site) {
+  const unsigned char* s = emu_wave_op(&v, sizeof(int), site, nullptr);
+  const int L = emu_cur->lane;
+  int from = L;
+  if (ctrl < 0x100) from = (L & ~3) | ((ctrl >> (2 * (L & 3))) & 3);
+  else if (ctrl > 0x120 && ctrl < 0x130) from = (L & 48) | ((L - (ctrl & 15)) & 15);
+  else if (ctrl == 0x140) from = (L & 48) | (15 - (L & 15));
+  else if (ctrl == 0x141) from = (L & 56) | (7 - (L & 7));
+  else __builtin_trap();
+  int r;
+  memcpy(&r, s + 64 * from, sizeof(int));
+  return r;
+}
+
+// ds_read_b64_tr_b16: within 16 lanes, lane 4 r + c points at columns 4 c .. 4 c + 3 of row r of a
+// 4 x 16 block of 16-bit values; lane j gets column j
+typedef short emu_s4 __attribute__((ext_vector_type(4)));
+static inline emu_s4 emu_ds_read_tr16(const void* p, int site) {
+  const unsigned char* s = emu_wave_op(p, 8, site, nullptr);
+  const int L = emu_cur->lane, j = L & 15;
+  emu_s4 o;
+  for (int r = 0; r < 4; ++r) o[r] = ((const short*)(s + 64 * ((L & 48) + 4 * r + (j >> 2))))[j & 3];
+  return o;
 }
 
 // v_mfma_f32_4x4x1_16b_f32: 16 blocks of 4 lanes; in block b (lanes 4b..4b+3) lane 4b+j,
