@@ -635,7 +635,7 @@ int split_mix(const Plan& p, int glo, int ghi, int r0, int n, const WsPlan& w, v
 // gW = S^T mbar over calls: split partials of every group (regions as ga_partials), summed on the last
 int split_ga(const Plan& p, int glo, int ghi, int r0, int n, const WsPlan& w, void* ws, const float* S,
              int64_t s_ncap, const float* M, float* gW, bool first_chunk, bool last_chunk, hipStream_t s) {
-  float* P = ga_partials(p, w, ws, glo);
+  float* P = ga_partials(p, w, ws, 0);   // the kernels step to their group's region
   int64_t blocks = 0, quads = 0;
   for (int i = glo; i < ghi; ++i) {
     const sobek::Group& g = p.groups[i];

@@ -19,12 +19,13 @@ def _n(t):
     return t.detach().cpu().numpy()
 
 
+@pytest.mark.parametrize("policy", ["all", "groups"])
 @pytest.mark.parametrize("i", range(len(sc.CASES)), ids=sc.IDS)
-def test_split_products(gpu, i):
+def test_split_products(gpu, i, policy):
     from paper_2607_18074_amd import api
     case = sc.case(i)
     irr_in, lmax, irr_out, K = case["sig"]
-    plan, g = api.Plan(irr_in, lmax, irr_out, K), case["graph"]
+    plan, g = api.Plan(irr_in, lmax, irr_out, K, policy=policy), case["graph"]
     graph = api.Graph(_t(g.rowptr), _t(g.sender))
     args = [_t(v) for v in (case["x"], g.evec, g.phi, case["W"])]
     oa = (oc.Problem(irr_in, lmax, irr_out, K), case["x"], g.evec, g.phi, case["W"], g.rowptr, g.sender)

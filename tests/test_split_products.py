@@ -9,12 +9,13 @@ from tests.emu import build as emu_build
 
 
 @pytest.mark.skipif(not emu_build.available(), reason="ROCm clang++ not found")
+@pytest.mark.parametrize("policy", ["all", "groups"])
 @pytest.mark.parametrize("i", range(len(sc.CASES)), ids=sc.IDS)
-def test_split_products(i):
+def test_split_products(i, policy):
     from tests.emu import harness as H
     case = sc.case(i)
     irr_in, lmax, irr_out, K = case["sig"]
-    plan, g = H.Plan(irr_in, lmax, irr_out, K), case["graph"]
+    plan, g = H.Plan(irr_in, lmax, irr_out, K, policy=policy), case["graph"]
     graph = H.Graph(g.rowptr, g.sender)
     args = [H.dev(v) for v in (case["x"], g.evec, g.phi, case["W"])]
     oa = (oc.Problem(irr_in, lmax, irr_out, K), case["x"], g.evec, g.phi, case["W"], g.rowptr, g.sender)
