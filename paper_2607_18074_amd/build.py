@@ -22,7 +22,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsobek_hip.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
-SOURCES = ["api.cpp", "plan.cpp", "split.cpp", "tables.cpp", "jit.cpp"]
+SOURCES = ["api.cpp", "plan.cpp", "split.cpp", "adjoint.cpp", "tables.cpp", "jit.cpp"]
 
 
 def _embed(name, delim):
@@ -40,6 +40,7 @@ def _embed(name, delim):
 def embed_prelude():
     _embed("prelude", "SOBEKPRELUDE")
     _embed("gemm_bf16", "SOBEKBF16")
+    _embed("adjoint", "SOBEKADJOINT")
     _embed("split", "SOBEKSPLIT")
 
 

@@ -28,10 +28,13 @@
 #include <memory>
 #include <mutex>
 #include <stdexcept>
+#include <sstream>
 #include <string>
 #include <vector>
 
 #include "../../include/sobek.h"
+#include "adjoint.h"
+#include "gen.h"
 #include "jit.h"
 #include "plan.h"
 #include "split.h"
@@ -695,6 +698,8 @@ int run_mix(const Plan& p, const Chunk& c, const WsPlan& w, void* ws, const floa
 // s_ncap receivers apart (the chunk slot, or a state kept for every receiver)
 int run_sbar(const Plan& p, const Chunk& c, int64_t s_ncap, const float* M, const float* W, float* Sbar,
              hipStream_t s) {
+  // column order: the k-table's, or [path, u][q] for the moment-form adjoint kernel (the table's second half)
+  const int32_t* ktab = p.d_ktab + (p.k.adj_bwd ? p.ktab.size() : 0);
   if (p.split) {
     // column tiles per block: all of a row block's when that gives about four blocks per CU, else fewer
     // (at least two, so that a block's mbar planes are used again)
@@ -707,7 +712,7 @@ int run_sbar(const Plan& p, const Chunk& c, int64_t s_ncap, const float* M, cons
       if (g.C <= 128) blocks += (int64_t)cdiv((int64_t)c.n * g.d, 128) * cdiv(cdiv(g.D, 64), tpb);
     int r0 = c.r0, n = c.n;
     long long cap = s_ncap;
-    LAUNCH(p.k.sp3_sbar, (unsigned)blocks, 1, 1, s, M, r0, n, W, (const int*)p.d_ktab, Sbar, cap, tpb);
+    LAUNCH(p.k.sp3_sbar, (unsigned)blocks, 1, 1, s, M, r0, n, W, (const int*)ktab, Sbar, cap, tpb);
   }
   for (auto& g : p.groups) {
     if (p.split && g.C <= 128) continue;
@@ -715,19 +720,19 @@ int run_sbar(const Plan& p, const Chunk& c, int64_t s_ncap, const float* M, cons
     int nrows = c.n * g.d, D = (int)g.D, dg = g.d, Cg = g.C, off = g.off, CX = p.dim_out, r0 = c.r0;
     if (p.mode == SOBEK_MODE_UVU)
       LAUNCH(p.k.uvu_sbar, cdiv((int64_t)nrows * D, 256), 1, 1, s, M, nrows, D, Cg, W,
-             (const int*)(p.d_ktab + g.ktab_off), Sg, dg, off, CX, r0);
+             (const int*)(ktab + g.ktab_off), Sg, dg, off, CX, r0);
     else if (sobek::sbar_streams(p.vec4, g.C))
     {
       // spread the 64-wide column tiles over blockIdx.y until about kSaTarget blocks run,
       // keeping at least four tiles per block
       const int rows = cdiv(nrows, sobek::sbar_block_rows(p, g.C)), ntile = cdiv(D, 64);
       const int gy = std::max(1, std::min((int)cdiv(kSaTarget, rows), ntile / 4));
-      LAUNCH(p.k.gemm_sbar_c.at(g.C), rows, gy, 1, s, M, nrows, D, W, (const int*)(p.d_ktab + g.ktab_off), Sg, dg,
+      LAUNCH(p.k.gemm_sbar_c.at(g.C), rows, gy, 1, s, M, nrows, D, W, (const int*)(ktab + g.ktab_off), Sg, dg,
              off, CX, r0);
     }
     else
       LAUNCH(p.k.gemm_sbar[2], cdiv(nrows, 64), cdiv(D, 64), 1, s, M, nrows, D, W,
-             (const int*)(p.d_ktab + g.ktab_off), Sg, dg, Cg, off, CX, r0);
+             (const int*)(ktab + g.ktab_off), Sg, dg, Cg, off, CX, r0);
   }
   return SOBEK_OK;
 }
@@ -903,6 +908,23 @@ int adj_edge_split(const Plan& p, int nr, int64_t ne) {
   return (int)std::max<int64_t>(1, std::min<int64_t>({cdiv(512, std::max(1, nr)), by_work, 64}));
 }
 
+// The moment-form adjoint kernel (device/adjoint.hip) over the receivers [ra, ra + nr) of one edge
+// window: a block per receiver and 64 of its edges (further 64s in the same block, or over blockIdx.y
+// when there are few receivers).  sb: adjoint state, group blocks sb_ncap receivers apart, receiver ra
+// at row sb_r0.  accum, accx: add to gphi and gevec, to contrib.
+int run_adjoint(const Plan& p, const sobek_graph_s& G, int64_t ea, int64_t eb, int ra, int nr, const float* x,
+                const float* evec, const float* phi, const float* sb, int64_t sb_ncap, int sb_r0, bool tangent,
+                const float* evdot, const float* phidot, int flags, float* gphi, float* gevec, float* contrib,
+                int accum, int accx, hipStream_t s) {
+  const int64_t ne = eb - ea;
+  const int gy = (int)std::max<int64_t>(1, std::min<int64_t>(cdiv(512, std::max(1, nr)), cdiv(ne, 64 * (int64_t)std::max(1, nr))));
+  int e0 = (int)ea, e1 = (int)eb;
+  long long ncap = sb_ncap;
+  LAUNCH_N(tangent ? p.k.adj_dbwd : p.k.adj_bwd, 512, nr, gy, 1, s, (const int*)G.rowptr, (const int*)G.sender, evec, phi,
+           x, sb, evdot, phidot, gphi, gevec, contrib, ra, e0, flags, ncap, sb_r0, e0, e1, accum, accx);
+  return SOBEK_OK;
+}
+
 int check_common(sobek_plan plan, sobek_graph graph, const float* x, const float* evec, const float* phi,
                  const float* W, void* ws, size_t ws_bytes) {
   if (!plan || !graph) return fail(SOBEK_E_INVALID, "NULL plan or graph");
@@ -992,17 +1014,33 @@ int load_receiver_route(Plan& p, hipModule_t m) {
   return SOBEK_OK;
 }
 
-// split channel products, a module of their own
-int load_split(Plan& p) {
-  if (!sobek::split_plan(p)) return SOBEK_OK;
+// split channel products and the moment-form adjoint kernels, a module of their own
+std::string aux_source(const Plan& p) {
+  const bool adj = sobek::adjoint_plan(p);
+  if (!sobek::split_plan(p) && !adj) return std::string();
+  std::ostringstream o;
+  o.precision(17);
+  o << sobek::generate_split_source(p);
+  if (adj) {
+    sobek::emit_sh(o, p.lmax);
+    o << sobek::generate_adjoint_source(p);
+  }
+  return o.str();
+}
+
+int load_aux(Plan& p) {
+  const std::string src = aux_source(p);
+  if (src.empty()) return SOBEK_OK;
+  const bool split = sobek::split_plan(p), adj = sobek::adjoint_plan(p);
   int rc;
-  if ((rc = load_module(sobek::generate_split_source(p), p.k.module_sp3))) return rc;
-  hipModule_t m = p.k.module_sp3;
-  if ((rc = get_fn(m, p.k.sp3_sa, "sobek_sp3_sa")) || (rc = get_fn(m, p.k.sp3_red, "sobek_sp3_red")) ||
-      (rc = get_fn(m, p.k.sp3_ga, "sobek_sp3_ga")) || (rc = get_fn(m, p.k.sp3_gared, "sobek_sp3_gared")) ||
-      (rc = get_fn(m, p.k.sp3_sbar, "sobek_sp3_sbar")))
+  if ((rc = load_module(src, p.k.module_aux))) return rc;
+  hipModule_t m = p.k.module_aux;
+  if (split && ((rc = get_fn(m, p.k.sp3_sa, "sobek_sp3_sa")) || (rc = get_fn(m, p.k.sp3_red, "sobek_sp3_red")) ||
+                (rc = get_fn(m, p.k.sp3_ga, "sobek_sp3_ga")) || (rc = get_fn(m, p.k.sp3_gared, "sobek_sp3_gared")) ||
+                (rc = get_fn(m, p.k.sp3_sbar, "sobek_sp3_sbar"))))
     return rc;
-  p.split = true;
+  if (adj && ((rc = get_fn(m, p.k.adj_bwd, "sobek_bwd_E")) || (rc = get_fn(m, p.k.adj_dbwd, "sobek_dbwd_E_r")))) return rc;
+  p.split = split;
   return SOBEK_OK;
 }
 
@@ -1155,9 +1193,18 @@ int sobek_plan_create(const sobek_irrep* in, int n_in, int lmax, const sobek_irr
     if ((rc = load_receiver_route(p, p.k.module))) return rc;
     p.rr_loaded = true;
   }
-  if ((rc = load_split(p))) return rc;
-  HIPCHK(hipMalloc(&p.d_ktab, std::max<size_t>(4, p.ktab.size() * 4)));
-  HIPCHK(hipMemcpy(p.d_ktab, p.ktab.data(), p.ktab.size() * 4, hipMemcpyHostToDevice));
+  if ((rc = load_aux(p))) return rc;
+  std::vector<int32_t> kt = p.ktab;   // then, for the moment-form adjoint kernel, with column koff + u K + q
+  if (sobek::adjoint_plan(p)) {
+    kt.insert(kt.end(), p.ktab.begin(), p.ktab.end());
+    for (auto& q : p.paths) {
+      const size_t k0 = p.groups[q.group].ktab_off + q.koff;
+      for (int u = 0; u < q.c_in; ++u)
+        for (int r = 0; r < p.K; ++r) kt[p.ktab.size() + k0 + (size_t)u * p.K + r] = p.ktab[k0 + (size_t)r * q.c_in + u];
+    }
+  }
+  HIPCHK(hipMalloc(&p.d_ktab, std::max<size_t>(4, kt.size() * 4)));
+  HIPCHK(hipMemcpy(p.d_ktab, kt.data(), kt.size() * 4, hipMemcpyHostToDevice));
   auto blocks = [](const std::vector<sobek::Irrep>& v) {
     std::vector<int32_t> b(3 * v.size());
     for (size_t i = 0; i < v.size(); ++i) {
@@ -1186,7 +1233,7 @@ int sobek_jit_compile(const sobek_irrep* in, int n_in, int lmax, const sobek_irr
     // SOBEK_JIT_STATE_FREE_ONLY=1: channelwise plans compile only the part a plan loads at creation
     const char* sf = std::getenv("SOBEK_JIT_STATE_FREE_ONLY");
     if (p.source_u.empty() || !sf || std::strcmp(sf, "1") != 0) sobek::jit_compile(p.source);
-    if (sobek::split_plan(p)) sobek::jit_compile(sobek::generate_split_source(p));
+    if (!aux_source(p).empty()) sobek::jit_compile(aux_source(p));
     if (materialized_supported(p)) sobek::jit_compile(sobek::generate_materialized_source(p));
     const char* gs = std::getenv("SOBEK_JIT_GROUPS");
     if (gs && std::strcmp(gs, "1") == 0) sobek::jit_compile(sobek::generate_group_source(p));
@@ -1260,7 +1307,7 @@ int sobek_plan_destroy(sobek_plan plan) {
   if (p.k.module_u) (void)hipModuleUnload(p.k.module_u);
   if (p.k.module_mat) (void)hipModuleUnload(p.k.module_mat);
   if (p.k.module_grp) (void)hipModuleUnload(p.k.module_grp);
-  if (p.k.module_sp3) (void)hipModuleUnload(p.k.module_sp3);
+  if (p.k.module_aux) (void)hipModuleUnload(p.k.module_aux);
   if (plan->side) (void)hipStreamDestroy(plan->side);
   if (plan->fork) (void)hipEventDestroy(plan->fork);
   if (plan->join) (void)hipEventDestroy(plan->join);
@@ -1585,6 +1632,11 @@ int conv_bwd_impl(sobek_plan plan, sobek_graph graph, const float* x, const floa
           if (p.uvu_NB * ns > 1 && (gphi || gevec))
             LAUNCH(p.k.uvu_bwd_fin, cdiv(eb - ea, 256), 1, 1, stream, evec, (const float*)part, gphi, gevec, e0, e1,
                    (const float*)nullptr);
+        } else if (p.k.adj_bwd) {
+          if (int r = run_adjoint(p, G, ea, eb, ra, nr, xk, evec, phi, adj_state ? adj_state : Sb,
+                                     adj_state ? G.N : w.ncap, adj_state ? ra : sub_off, false, nullptr, nullptr, 0, gphi,
+                                     gevec, contrib, 0, 0, stream))
+            return r;
         } else {
           long long ncap = w.ncap, sb_ncap = adj_state ? G.N : w.ncap;
           int sb_r0 = adj_state ? ra : sub_off;
@@ -1927,6 +1979,29 @@ int conv_dbwd_impl(sobek_plan plan, sobek_graph graph, const float* x, const flo
       if (t_gW && (rc = run_sbar(p, c, w.ncap, gk, t_gW, Sb2, stream))) return rc;
       rc = for_edge_windows(G, c, w, [&](int64_t ea, int64_t eb, int ra, int nr) -> int {
         int e0 = (int)ea, e1 = (int)eb, fl = flags, sub_off = ra - c.r0;
+        if (p.k.adj_bwd) {
+          // the tangent of phi Y with x; then the terms of the x tangent and of the weight cotangent, each
+          // the backward's edge terms with (xdot, Sbar) and (x, Sbar')
+          const float* sb = adj_state ? adj_state : Sb;
+          const int64_t cap = adj_state ? G.N : w.ncap;
+          const int row = adj_state ? ra : sub_off;
+          int n = 0, r = SOBEK_OK;
+          if ((flags & 5) && (r = run_adjoint(p, G, ea, eb, ra, nr, xk, evec, phi, sb, cap, row, true, t_gevec, t_gphi,
+                                                 flags, g_phi, g_evec, contrib, n++, 0, stream)))
+            return r;
+          if ((flags & 2) && (g_phi || g_evec) &&
+              (r = run_adjoint(p, G, ea, eb, ra, nr, txk, evec, phi, sb, cap, row, false, nullptr, nullptr, 0, g_phi,
+                                  g_evec, nullptr, n++, 0, stream)))
+            return r;
+          if ((flags & 8) &&
+              (r = run_adjoint(p, G, ea, eb, ra, nr, xk, evec, phi, Sb2, w.ncap, sub_off, false, nullptr, nullptr, 0,
+                                  g_phi, g_evec, contrib, n++, (flags & 5) ? 1 : 0, stream)))
+            return r;
+          if (!(flags & 13)) return SOBEK_OK;   // no x-gradient term: zero rows, written after the windows
+          const int first = first_win;
+          first_win = false;
+          return g_x ? run_sender_reduce(p, G, ea, eb, w, ws, contrib, gxk, first, stream) : SOBEK_OK;
+        }
         long long ncap = w.ncap, sb_ncap = adj_state ? G.N : w.ncap;
         int sb_r0 = adj_state ? ra : sub_off;
         LAUNCH_N(flags == 4 ? p.k.dbwd_E_r : p.k.dbwd_E, 64 * p.adj_waves, nr, adj_edge_split(p, nr, eb - ea), 1,

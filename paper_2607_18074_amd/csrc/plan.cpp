@@ -11,6 +11,7 @@
 #include <sstream>
 #include <stdexcept>
 
+#include "gen.h"
 #include "plan.h"
 #include "tables.h"
 
@@ -235,13 +236,13 @@ void build_plan(Plan& p) {
 // ---------------------------------------------------------------------------
 // code generation
 // ---------------------------------------------------------------------------
-namespace {
-
 std::string fl(double v) {
   char b[64];
   std::snprintf(b, sizeof(b), "%.9e", v);
   return std::string(b) + "f";
 }
+
+namespace {
 
 std::string mono(int px, int py, int pz) {
   std::string s;
@@ -287,6 +288,8 @@ std::string powers(int L) {
       << "*z; (void)x" << k << "; (void)y" << k << "; (void)z" << k << ";\n";
   return o.str();
 }
+
+}  // namespace
 
 void emit_sh(std::ostringstream& o, int lmax) {
   // Y[0 .. (L+1)^2) on the unit sphere
@@ -355,15 +358,6 @@ void emit_sh(std::ostringstream& o, int lmax) {
        "  h[2] = (t1z - t2z*ud - z*t3 - dz*t4 + z*ud*t5)*r2;\n}\n";
 }
 
-struct PairTerm { int my; double c; };
-
-// Sparse structure of a path's coupling: the (m_i, m_o) pairs with a nonzero
-// coefficient, each with its (m_y, c) terms.
-struct PathTerms {
-  std::vector<std::pair<int, int>> pairs;
-  std::vector<std::vector<PairTerm>> terms;
-};
-
 PathTerms path_terms(const Path& q) {
   const int di = 2 * q.l_in + 1, ds = 2 * q.l_sh + 1, dd = 2 * q.l_out + 1;
   PathTerms r;
@@ -378,6 +372,8 @@ PathTerms path_terms(const Path& q) {
     }
   return r;
 }
+
+namespace {
 
 // Path p: M[(mi,mo) pairs] = sum_my c Y[my];  C[mo] = sum_mi x[mi] M[mi,mo].
 void emit_path(std::ostringstream& o, const Plan& P, int t) {

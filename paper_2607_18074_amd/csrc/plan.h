@@ -89,7 +89,8 @@ struct Kernels {
   std::vector<std::array<hipFunction_t, 3>> fwd_grp;  // per group: S, dS_r, dS
   hipModule_t module_mat = nullptr;  // the materialized-forward baseline (compiled on first use)
   hipFunction_t mat_w = nullptr, mat_msg = nullptr, mat_reduce = nullptr;
-  hipModule_t module_sp3 = nullptr;  // split channel products (split_plan)
+  hipModule_t module_aux = nullptr;  // split channel products, moment-form adjoint (split_plan, adjoint_plan)
+  hipFunction_t adj_bwd = nullptr, adj_dbwd = nullptr;
   hipFunction_t sp3_sa = nullptr, sp3_red = nullptr, sp3_ga = nullptr, sp3_gared = nullptr, sp3_sbar = nullptr;
   hipModule_t module_u = nullptr;  // channelwise plans: the state-free kernels and the common ones
   hipFunction_t fwd_S = nullptr, fwd_dS = nullptr, fwd_dS_r = nullptr;

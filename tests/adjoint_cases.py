@@ -1,0 +1,43 @@
+"""Cases of the moment-form adjoint kernels (inputs only), shared by their CPU and GPU tests.
+
+Receivers without edges, with one, and with counts on both sides of the 16-edge tile and the 64-edge
+pass; an odd and an even number of spherical-harmonic components; groups of an odd and an even number of
+slots, channel blocks of one, two and four 16-channel tiles, input irreps that no path reads, channel
+counts of the adjoint-state products that are no multiple of their tiles.
+"""
+
+import numpy as np
+
+from paper_2607_18074_amd import workloads as wl
+from tests.cases import make_case
+
+DEGREES = (0, 1, 15, 0, 16, 17, 63, 2, 64, 65, 129)
+
+# (irreps in, lmax, irreps out, K)
+SIGS = [
+    ("64x0e+64x1o+64x2e", 2, "16x0e+16x1o+12x2e", 16),             # 9 components, narrow blocks
+    ("80x1o+48x2e+16x3o+16x0e", 3, "20x0e+16x1o", 16),             # 7 slots of one irrep; 16-channel tails
+    ("64x0e+64x1o+64x1e+64x2e+32x0o", 3, "16x0e+16x1o+16x2e", 16),  # no path reads 32x0o; 64-channel blocks
+]
+IDS = [s[0] for s in SIGS]
+
+# An edge term is a sum over paths, radial features and channels of products whose operands keep 2^-25 in
+# three bf16 parts (six products: 3 x 2^-25 a term); a 32-deep step adds one fp32 rounding.  The longest
+# sums here have n = 16 x 192 x 9 terms: sqrt(n) 2^-24 = 1e-5 of their norm is the bound of unlucky signs.
+TOL = 1e-5
+
+
+def case(i, degrees=DEGREES):
+    c = make_case(SIGS[i], len(degrees), int(np.sum(degrees)), 500 + i)
+    g = c["graph"]
+    rowptr = np.concatenate([[0], np.cumsum(degrees)]).astype(np.int32)
+    c["graph"] = wl.Graph(g.N, rowptr, g.sender, g.evec, g.phi)
+    return c
+
+
+# cotangents of the double backward: each term alone, pairs that share an output, all
+COTANGENTS = [("evec",), ("x",), ("phi",), ("W",), ("x", "W"), ("x", "evec", "phi", "W")]
+
+
+def cotangents(case, which):
+    return {k: (v if k in which else None) for k, v in case["cot"].items()}

@@ -1,7 +1,7 @@
 """Build of the CPU emulation library (test infrastructure; never loaded by the package).
 
-libsobek_emu.so is the library's own host code (csrc/api.cpp, plan.cpp, split.cpp, tables.cpp) compiled for
-the host against a stand-in HIP runtime (hip/hip_runtime.h, mock_hip.cpp) and a plan compiler
+libsobek_emu.so is the library's own host code (csrc/api.cpp, plan.cpp, split.cpp, adjoint.cpp, tables.cpp)
+compiled for the host against a stand-in HIP runtime (hip/hip_runtime.h, mock_hip.cpp) and a plan compiler
 that builds the generated kernels for the host (mock_jit.cpp, emu_device.h).  Outputs go to
 tests/emu/_build (or _build_asan for the AddressSanitizer variant).
 """
@@ -33,7 +33,7 @@ def build(asan=False, force=False):
     pkg_build.embed_prelude()   # the device prelude the plan compiler embeds (a generated header)
     out = out_dir(asan)
     lib = os.path.join(out, "libsobek_emu.so")
-    units = [os.path.join(CSRC, f) for f in ("api.cpp", "plan.cpp", "split.cpp", "tables.cpp")] + \
+    units = [os.path.join(CSRC, f) for f in ("api.cpp", "plan.cpp", "split.cpp", "adjoint.cpp", "tables.cpp")] + \
             [os.path.join(HERE, f) for f in ("mock_jit.cpp", "mock_hip.cpp")]
     deps = units + [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".h", ".inc"))] + \
         [os.path.join(HERE, f) for f in ("emu_rt.h", "emu_device.h", os.path.join("hip", "hip_runtime.h"))] + \

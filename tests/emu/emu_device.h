@@ -35,6 +35,7 @@
 #define __builtin_amdgcn_readfirstlane(v) (v)
 #define __builtin_amdgcn_mov_dpp(v, ctrl, rm, bm, bc) emu_mov_dpp((v), (ctrl), __LINE__)
 #define __builtin_amdgcn_ds_read_tr16_b64_v4i16(p) emu_ds_read_tr16((const void*)(uintptr_t)(p), __LINE__)
+#define SBA_SCALAR(p) ((void)0)   // scalar-register hint of the adjoint kernels
 #define __ballot(p) emu_ballot((p), __LINE__)
 #define __shfl_xor(...) emu_shfl_xor_(__LINE__, __VA_ARGS__)
 #define __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, x, y, z) emu_mfma_4x4x1((a), (b), (c), __LINE__)

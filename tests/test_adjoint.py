@@ -1,0 +1,31 @@
+"""The moment-form adjoint kernels on the CPU emulation build, against the float64 oracle."""
+
+import numpy as np
+import pytest
+
+from oracle import conv as oc
+from tests import adjoint_cases as ac
+from tests.cases import max_rel
+from tests.emu import build as emu_build
+
+
+@pytest.mark.skipif(not emu_build.available(), reason="ROCm clang++ not found")
+def test_adjoint():
+    from tests.emu import harness as H
+    case = ac.case(0, (0, 65))
+    irr_in, lmax, irr_out, K = case["sig"]
+    plan, g = H.Plan(irr_in, lmax, irr_out, K), case["graph"]
+    graph = H.Graph(g.rowptr, g.sender)
+    args, gout = [H.dev(v) for v in (case["x"], g.evec, g.phi, case["W"])], H.dev(case["gout"])
+    oa = (oc.Problem(irr_in, lmax, irr_out, K), case["x"], g.evec, g.phi, case["W"], g.rowptr, g.sender)
+    ref = oc.bwd(*oa, case["gout"])
+    outs = H.conv_bwd(plan, graph, *args, gout, need=(True, True, True, False))
+    for name, o in zip(("gx", "gevec", "gphi"), outs):
+        assert max_rel(o.np(), ref[name]) <= ac.TOL, name
+    t = case["cot"]
+    ref = oc.dbwd(*oa, case["gout"], t_gx=t["x"], t_gevec=t["evec"], t_gphi=t["phi"], t_gW=t["W"])
+    outs = H.conv_dbwd(plan, graph, *args, gout, *[H.dev(t[k]) for k in ("x", "evec", "phi", "W")],
+                        need=(False, True, True, True, False))
+    for name, o in zip(("g_x", "g_evec", "g_phi"), outs[1:4]):
+        assert max_rel(o.np(), ref[name]) <= ac.TOL, name
+        assert np.isfinite(o.np()).all()
