@@ -433,6 +433,7 @@ PAPER_CONTEXT = {
 
 
 def kernel_kind(name):
+    name = name.replace("sobek_sp3_", "sobek_gemm_")   # the channel products on split operands
     for k in ("fwd_dS", "fwd_S", "bwd_E", "dbwd_E", "gemm_sa", "gemm_sbar", "gemm_ga"):
         if name == "sobek_" + k or name.startswith("sobek_" + k + "_"):
             return k
