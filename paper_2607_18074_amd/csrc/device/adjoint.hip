@@ -22,9 +22,9 @@
 // is a step's chain (load, form and split, barrier, LDS reads, six dependent products), about 1 us with
 // two waves a SIMD; without the products a receiver of four edges still takes four fifths of the time.
 // Edge time of one backward, per-edge kernel before and this one now:
-//   64x0e+64x1o+64x1e+64x2e lmax 3, 20,000 receivers, 1,000,000 edges     13.3 -> 8.1 ms
+//   64x0e+64x1o+64x1e+64x2e lmax 3, 20,000 receivers, 1,000,000 edges     13.3 -> 7.8 ms
 //   128x0e+128x1o+128x2e+64x3o lmax 3, 480,000 edges                      14.3 -> 11.1 ms
-//   its radius-only double backward, first plan                           12.3 -> 8.4 ms
+//   its radius-only double backward, first plan                           12.3 -> 8.3 ms
 
 #define SBA_BLK 640                         // bytes of one (m_y, slot): [q octet][u][8 q], octets 320 apart
 #define SBA_NC ((NSH + 1) / 2)              // steps per channel tile: two m_y each
@@ -69,65 +69,65 @@ SB_DEV sbm_f4 sba_ld4(const float* __restrict__ base, unsigned off) {
 }
 
 // One step's products for a wave (column half hf): xbar of its slots, T of its m_y (NMY: m_y of the step).
+// Chains of six run in twos; the odd ones of xbar and T go together (apart, their latencies added up:
+// 8.1 -> 7.8 ms in the first case above).
 template <int SL, int NMY>
 SB_DEV void sba_step(const char* buf, int j, int g, int hf, bool has_x, const sbm_b8* phi_planes,
                      const sbm_p3 (&xp)[(SL + 1) / 2], sbm_f4 (&xacc)[(SL + 1) / 2], sbm_f4& T) {
   constexpr int PL = 2 * SL * SBA_BLK, SH = (SL + 1) / 2;
+  // a step of one m_y: its phi Y is zero in the other's places, which read the first one's values
+  const char* bx = buf + min(g >> 1, NMY - 1) * (SL * SBA_BLK) + (g & 1) * 320 + j * 16;
+  auto xop = [&](int s) {
+    const char* bs = bx + min(hf * SH + s, SL - 1) * SBA_BLK;
+    sbm_p3 B;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) B.p[p] = *(const sbm_b8*)(bs + p * PL);
+    return B;
+  };
+  const int row = j >> 2, c = j & 3;
+  const char* bt = buf + min(hf, NMY - 1) * (SL * SBA_BLK) + (c >> 1) * 320 + (8 * (g & 1) + row) * 16 + (c & 1) * 8;
+  auto top = [&](int s) {
+    const char* bs = bt + min(2 * s + (g >> 1), SL - 1) * SBA_BLK;
+    sbm_p3 B;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const sbm_b4 lo = sbm_tr4(bs + p * PL), hi = sbm_tr4(bs + p * PL + 64);
+      B.p[p] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+    return B;
+  };
+  sbm_p3 pa;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) pa.p[p] = phi_planes[p * 64];
   if (has_x) {
-    sbm_p3 pa;
 #pragma unroll
-    for (int p = 0; p < 3; ++p) pa.p[p] = phi_planes[p * 64];
-    // a step of one m_y: its phi Y is zero in the other's places, which read the first one's values
-    const char* b = buf + min(g >> 1, NMY - 1) * (SL * SBA_BLK) + (g & 1) * 320 + j * 16;
-#pragma unroll
-    for (int s = 0; s < SH; s += 2) {
-      sbm_p3 B[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-        if (s + h < SH) {
-          const char* bs = b + min(hf * SH + s + h, SL - 1) * SBA_BLK;
-#pragma unroll
-          for (int p = 0; p < 3; ++p) B[h].p[p] = *(const sbm_b8*)(bs + p * PL);
-        }
+    for (int s = 0; s + 1 < SH; s += 2) {
+      const sbm_p3 B0 = xop(s), B1 = xop(s + 1);
       sbm_f4 v0 = {0.f, 0.f, 0.f, 0.f}, v1 = {0.f, 0.f, 0.f, 0.f};
-      if (s + 1 < SH) {
-        sba_six2(v0, v1, B[0], pa, B[1], pa);
-        xacc[s + 1 < SH ? s + 1 : 0] += v1;
-      } else {
-        constexpr int q0[6] = {2, 0, 1, 1, 0, 0}, q1[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-        for (int n = 0; n < 6; ++n) v0 = sbm_mfma(B[0].p[q0[n]], pa.p[q1[n]], v0);
-      }
+      sba_six2(v0, v1, B0, pa, B1, pa);
       xacc[s] += v0;
+      xacc[s + 1] += v1;
     }
   }
-  if (hf < NMY) {
-    const int row = j >> 2, c = j & 3;
-    const char* b = buf + hf * (SL * SBA_BLK) + (c >> 1) * 320 + (8 * (g & 1) + row) * 16 + (c & 1) * 8;
+  const bool has_t = hf < NMY;
+  sbm_f4 t = {0.f, 0.f, 0.f, 0.f};
+  if (has_t) {
+#pragma unroll
+    for (int s = 0; s + 1 < SH; s += 2) {
+      const sbm_p3 B0 = top(s), B1 = top(s + 1);
+      sbm_f4 v0 = {0.f, 0.f, 0.f, 0.f}, v1 = {0.f, 0.f, 0.f, 0.f};
+      sba_six2(v0, v1, B0, xp[s], B1, xp[s + 1]);
+      t += v0 + v1;
+    }
+  }
+  if (SH % 2) {   // both, whether or not each is wanted
+    const sbm_p3 B0 = xop(SH - 1), B1 = top(SH - 1);
     sbm_f4 v0 = {0.f, 0.f, 0.f, 0.f}, v1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < SH; s += 2) {
-      sbm_p3 B[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-        if (s + h < SH) {
-          const char* bs = b + min(2 * (s + h) + (g >> 1), SL - 1) * SBA_BLK;
-#pragma unroll
-          for (int p = 0; p < 3; ++p) {
-            const sbm_b4 lo = sbm_tr4(bs + p * PL), hi = sbm_tr4(bs + p * PL + 64);
-            B[h].p[p] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          }
-        }
-      if (s + 1 < SH) {
-        sba_six2(v0, v1, B[0], xp[s], B[1], xp[s + 1 < SH ? s + 1 : 0]);
-      } else {
-        constexpr int q0[6] = {2, 0, 1, 1, 0, 0}, q1[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-        for (int n = 0; n < 6; ++n) v0 = sbm_mfma(B[0].p[q0[n]], xp[s].p[q1[n]], v0);
-      }
-    }
-    T += v0 + v1;
+    sba_six2(v0, v1, B0, pa, B1, xp[SH - 1]);
+    xacc[SH - 1] += v0;
+    t += v1;
   }
+  if (has_t) T += t;
 }
 
 // Edge outputs of a wave's m_y (2 c + hf): lane (edge j, g) holds T[c][r] of q = 4 g + r.  The other
