@@ -483,9 +483,12 @@ struct Ctx {
 };
 
 int fill_zero(const Plan& p, float* buf, int64_t n, hipStream_t s) {
-  if (!buf || n <= 0) return SOBEK_OK;
-  long long nn = n;
-  LAUNCH(p.k.zero, cdiv(n, 256), 1, 1, s, buf, nn);
+  if (!buf) return SOBEK_OK;
+  constexpr int64_t most = (int64_t)1 << 30;   // a launch holds fewer than 2^32 threads
+  for (int64_t o = 0; o < n; o += most) {
+    long long nn = std::min(most, n - o);
+    LAUNCH(p.k.zero, cdiv(nn, 256), 1, 1, s, buf + o, nn);
+  }
   return SOBEK_OK;
 }
 
@@ -1878,6 +1881,13 @@ int conv_dbwd_impl(sobek_plan plan, sobek_graph graph, const float* x, const flo
   const bool tan = flags & 7;
   if (g_W) { if ((rc = fill_zero(p, g_W, (int64_t)p.K * p.n_w, stream))) return rc; }
   if (G.N == 0) return SOBEK_OK;
+  // no cotangent: every output is zero (the moment-form kernels have no pass of their own that writes one)
+  if (!flags) {
+    if ((rc = fill_zero(p, g_gout, G.N * p.dim_out, stream)) || (rc = fill_zero(p, g_x, G.N * p.dim_in, stream)) ||
+        (rc = fill_zero(p, g_evec, G.E * 3, stream)) || (rc = fill_zero(p, g_phi, G.E * p.K, stream)))
+      return rc;
+    return SOBEK_OK;
+  }
   const bool mulir = p.layout == SOBEK_LAYOUT_MUL_IR;
   const float *xk = x, *gk = gout, *txk = t_gx;
   float *ggk = g_gout, *gxk = g_x;
@@ -1893,7 +1903,6 @@ int conv_dbwd_impl(sobek_plan plan, sobek_graph graph, const float* x, const flo
     if (g_gout) ggk = (float*)((char*)ws + w.off_out);
     if (g_x) gxk = (float*)((char*)ws + w.off_gx);
   }
-  if (g_gout && !tan && !t_gW) { if ((rc = fill_zero(p, ggk, G.N * p.dim_out, stream))) return rc; }
   if (uvu_free) {
     int n = (int)G.N, r0 = 0;
     if (g_gout) {

@@ -35,8 +35,8 @@ def case(i, degrees=DEGREES):
     return c
 
 
-# cotangents of the double backward: each term alone, pairs that share an output, all
-COTANGENTS = [("evec",), ("x",), ("phi",), ("W",), ("x", "W"), ("x", "evec", "phi", "W")]
+# cotangents of the double backward: none, each term alone, pairs that share an output, all
+COTANGENTS = [(), ("evec",), ("x",), ("phi",), ("W",), ("x", "W"), ("x", "evec", "phi", "W")]
 
 
 def cotangents(case, which):

@@ -26,6 +26,7 @@ def _check(outs, ref, names, what):
 
 @pytest.mark.parametrize("i", range(len(ac.SIGS)), ids=ac.IDS)
 def test_adjoint(gpu, i):
+    import torch
     from paper_2607_18074_amd import api
     case = ac.case(i)
     irr_in, lmax, irr_out, K = case["sig"]
@@ -43,5 +44,59 @@ def test_adjoint(gpu, i):
         t = ac.cotangents(case, which)
         ref = oc.dbwd(*oa, case["gout"], t_gx=t["x"], t_gevec=t["evec"], t_gphi=t["phi"], t_gW=t["W"])
         for kw in (dict(), dict(adj_state=adj), dict(budget=1 << 21)):
+            # memory that the outputs may be given: not zero by chance
+            poison = [torch.full(s, float("nan"), device="cuda") for s in
+                      ((g.N, plan.dim_out), (g.N, plan.dim_in), (g.E, 3), (g.E, K), (K, plan.n_weights))]
+            del poison
             outs = api.conv_dbwd(plan, graph, *args, gout, *[_t(t[k]) for k in ("x", "evec", "phi", "W")], **kw)
             _check(outs, ref, ("g_gout", "g_x", "g_evec", "g_phi", "g_W"), (which, list(kw)))
+
+
+def _autograd_case():
+    import torch
+    from paper_2607_18074_amd import api
+    case = ac.case(0, (3, 0, 20, 65))
+    irr_in, lmax, irr_out, K = case["sig"]
+    plan, g = api.Plan(irr_in, lmax, irr_out, K), case["graph"]
+    graph = api.Graph(_t(g.rowptr), _t(g.sender))
+    oa = (oc.Problem(irr_in, lmax, irr_out, K), case["x"], g.evec, g.phi, case["W"], g.rowptr, g.sender)
+    return torch, api, plan, graph, case, [_t(v) for v in (case["x"], g.evec, g.phi, case["W"])], oa
+
+
+@pytest.mark.parametrize("retain", [False, True])
+def test_autograd_of_some_inputs(gpu, retain):
+    """Inputs without gradients (phi, W), and a loss on one of the first gradients."""
+    torch, api, plan, graph, case, args, oa = _autograd_case()
+    x, ev = args[0].requires_grad_(), args[1].requires_grad_()
+    gout = _t(case["gout"])
+    m = api.tp_conv(plan, graph, *args, retain_state=retain)
+    gx, gev = torch.autograd.grad(m, (x, ev), gout, create_graph=True)
+    ref = oc.bwd(*oa, case["gout"])
+    _check((gx, gev), ref, ("gx", "gevec"), "first")
+    d = torch.autograd.grad((gev ** 2).sum(), (x, ev))
+    ref = oc.dbwd(*oa, case["gout"], t_gevec=2 * gev.detach().cpu().numpy().astype(np.float64))
+    _check(d, ref, ("g_x", "g_evec"), "second")
+
+
+def test_autograd_without_cotangents(gpu):
+    """A node downstream that returns no gradient: the double backward is called with none and gives zeros."""
+    torch, api, plan, graph, case, args, oa = _autograd_case()
+
+    class Drop(torch.autograd.Function):
+        @staticmethod
+        def forward(ctx, a):
+            return a.clone()
+
+        @staticmethod
+        def backward(ctx, g):
+            return None
+
+    for a in args:
+        a.requires_grad_()
+    m = api.tp_conv(plan, graph, *args)
+    g1 = torch.autograd.grad(m, args, _t(case["gout"]), create_graph=True)
+    loss = sum(Drop.apply(v).sum() for v in g1)
+    poison = [torch.full_like(a, float("nan")) for a in args]
+    del poison
+    for a, d in zip(args, torch.autograd.grad(loss, args, allow_unused=True)):
+        assert d is None or float(d.abs().max()) == 0
