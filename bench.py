@@ -434,6 +434,7 @@ PAPER_CONTEXT = {
 
 def kernel_kind(name):
     name = name.replace("sobek_sp3_", "sobek_gemm_")   # the channel products on split operands
+    name = name.replace("sobek_adj_dE", "sobek_dbwd_E").replace("sobek_adj_E", "sobek_bwd_E")   # moment form
     for k in ("fwd_dS", "fwd_S", "bwd_E", "dbwd_E", "gemm_sa", "gemm_sbar", "gemm_ga"):
         if name == "sobek_" + k or name.startswith("sobek_" + k + "_"):
             return k

@@ -295,7 +295,7 @@ std::string generate_adjoint_source(const Plan& p) {
        "  }\n}\n";
   for (int db = 0; db < 2; ++db)
     o << "extern \"C\" __global__ __launch_bounds__(SBA_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void "
-      << (db ? "sobek_dbwd_E_r" : "sobek_bwd_E")
+      << (db ? "sobek_adj_dE" : "sobek_adj_E")
       << "(const int* __restrict__ rowptr, const int* __restrict__ sender, const float* __restrict__ evec,"
          " const float* __restrict__ phi, const float* __restrict__ x, const float* __restrict__ Sb,"
          " const float* __restrict__ evdot, const float* __restrict__ phidot, float* __restrict__ gphi,"

@@ -6,14 +6,14 @@
 //                            m_g = S_g A_g                      [sobek_gemm_sa, per output group]
 //   backward (Section 4.3):  Sbar_g = mbar_g A_g^T              [sobek_gemm_sbar]
 //                            A_bar_g += S_g^T mbar_g            [sobek_gemm_ga + sobek_ga_reduce]
-//                            phi_bar, evec_bar, per-edge x contributions   [sobek_bwd_E]
+//                            phi_bar, evec_bar, per-edge x contributions   [sobek_bwd_E, or sobek_adj_E]
 //                            x_bar via the sender-sorted view   [sobek_sender_reduce]
 //   double backward (Section 4.4, eq. receiver_double_adjoint with d mbar = 0):
 //                            dS (directional state)             [sobek_fwd_dS]
 //                            m_dot = dS A + S dA                [sobek_gemm_sa x2]
 //                            Sbar = mbar A^T, Sbar' = mbar dA^T [sobek_gemm_sbar x2]
 //                            g_A = dS^T mbar                    [sobek_gemm_ga]
-//                            edge-local second adjoints         [sobek_dbwd_E]
+//                            edge-local second adjoints         [sobek_dbwd_E, or sobek_adj_dE, sobek_adj_E]
 //                            g_x via the sender-sorted view     [sobek_sender_reduce]
 // Every reduction has a fixed order (CSR order, split order, chunk order), so
 // results are bitwise reproducible for a given workspace size.
@@ -1042,7 +1042,7 @@ int load_aux(Plan& p) {
                 (rc = get_fn(m, p.k.sp3_ga, "sobek_sp3_ga")) || (rc = get_fn(m, p.k.sp3_gared, "sobek_sp3_gared")) ||
                 (rc = get_fn(m, p.k.sp3_sbar, "sobek_sp3_sbar"))))
     return rc;
-  if (adj && ((rc = get_fn(m, p.k.adj_bwd, "sobek_bwd_E")) || (rc = get_fn(m, p.k.adj_dbwd, "sobek_dbwd_E_r")))) return rc;
+  if (adj && ((rc = get_fn(m, p.k.adj_bwd, "sobek_adj_E")) || (rc = get_fn(m, p.k.adj_dbwd, "sobek_adj_dE")))) return rc;
   p.split = split;
   return SOBEK_OK;
 }

@@ -27,7 +27,7 @@ def _check(outs, ref, names, what):
 @pytest.mark.parametrize("i", range(len(ac.SIGS)), ids=ac.IDS)
 def test_adjoint(gpu, i):
     import torch
-    from paper_2607_18074_amd import api
+    from paper_2607_18074_amd import _lib, api
     case = ac.case(i)
     irr_in, lmax, irr_out, K = case["sig"]
     plan, g = api.Plan(irr_in, lmax, irr_out, K), case["graph"]
@@ -37,6 +37,13 @@ def test_adjoint(gpu, i):
     ref = oc.bwd(*oa, case["gout"])
     adj = api.new_state(plan, graph)
     adj.fill_(float("nan"))
+    _lib.profile_reset()
+    _lib.profile_enable(True)
+    api.conv_bwd(plan, graph, *args, gout, budget=0)
+    api.conv_dbwd(plan, graph, *args, gout, t_gevec=_t(case["cot"]["evec"]))
+    ran = set(_lib.profile_read())
+    _lib.profile_enable(False)
+    assert {"sobek_adj_E", "sobek_adj_dE"} <= ran and not ran & {"sobek_bwd_E", "sobek_dbwd_E_r", "sobek_dbwd_E"}
     for budget in (0, 1 << 21):   # one chunk of receivers; several
         _check(api.conv_bwd(plan, graph, *args, gout, budget=budget), ref, ("gx", "gevec", "gphi", "gW"), budget)
     _check(api.conv_bwd(plan, graph, *args, gout, adj_state=adj), ref, ("gx", "gevec", "gphi", "gW"), "kept")
