@@ -49,15 +49,20 @@ std::vector<AdjGroup> pack_groups(const Plan& p, int block) {
 }  // namespace
 
 // Channel blocks of 64, or narrower where that packs the slots into fewer steps (each costs a barrier
-// and the latency of its products whatever it holds).
+// and the latency of its products whatever it holds).  A group's steps over m_y are written out, its
+// channel tiles are a loop, and the compiler moves loads ahead through what is written out: 16 to 40 steps
+// spill up to 81 registers, the 88 of 128x0e+64x1o+64x2e+64x3o in blocks of 16 (eleven groups of one tile)
+// 6,970, and its 96 steps in blocks of 64, 24 of them written out, 57.  Backward of 700 receivers, degree 64:
+// 3.88 ms and 1.02 ms (per-edge kernels 1.34 ms).  A narrower block is taken up to kWritten only.
 std::vector<AdjGroup> adjoint_groups(const Plan& p) {
+  const int kWritten = 48, NC = (p.nsh + 1) / 2;
   std::vector<AdjGroup> best;
   int fewest = 0;
   for (int block = 64; block >= 16; block /= 2) {
     std::vector<AdjGroup> gs = pack_groups(p, block);
     int steps = 0;
     for (auto& g : gs) steps += g.UT;
-    if (best.empty() || steps < fewest) {
+    if (best.empty() || (steps < fewest && (int)gs.size() * NC <= kWritten)) {
       best = gs;
       fewest = steps;
     }

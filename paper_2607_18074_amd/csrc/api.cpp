@@ -1042,7 +1042,20 @@ int load_aux(Plan& p) {
                 (rc = get_fn(m, p.k.sp3_ga, "sobek_sp3_ga")) || (rc = get_fn(m, p.k.sp3_gared, "sobek_sp3_gared")) ||
                 (rc = get_fn(m, p.k.sp3_sbar, "sobek_sp3_sbar"))))
     return rc;
-  if (adj && ((rc = get_fn(m, p.k.adj_bwd, "sobek_adj_E")) || (rc = get_fn(m, p.k.adj_dbwd, "sobek_adj_dE")))) return rc;
+  if (adj) {
+    // the moment form is taken unless it spills: up to 320 bytes a lane it takes 0.4 to 1.1 times the per-edge
+    // kernels' time, with 1,244 (128x0e+64x1o+64x2e+64x3o, all its steps written out) 1.5 to 3.5 times
+    const int most = 512;
+    int sb = 0, sd = 0;
+    hipFunction_t fb = nullptr, fd = nullptr;
+    if ((rc = get_fn(m, fb, "sobek_adj_E")) || (rc = get_fn(m, fd, "sobek_adj_dE"))) return rc;
+    HIPCHK(hipFuncGetAttribute(&sb, HIP_FUNC_ATTRIBUTE_LOCAL_SIZE_BYTES, fb));
+    HIPCHK(hipFuncGetAttribute(&sd, HIP_FUNC_ATTRIBUTE_LOCAL_SIZE_BYTES, fd));
+    if (std::max(sb, sd) <= most) {
+      p.k.adj_bwd = fb;
+      p.k.adj_dbwd = fd;
+    }
+  }
   p.split = split;
   return SOBEK_OK;
 }
@@ -1198,7 +1211,7 @@ int sobek_plan_create(const sobek_irrep* in, int n_in, int lmax, const sobek_irr
   }
   if ((rc = load_aux(p))) return rc;
   std::vector<int32_t> kt = p.ktab;   // then, for the moment-form adjoint kernel, with column koff + u K + q
-  if (sobek::adjoint_plan(p)) {
+  if (p.k.adj_bwd) {
     kt.insert(kt.end(), p.ktab.begin(), p.ktab.end());
     for (auto& q : p.paths) {
       const size_t k0 = p.groups[q.group].ktab_off + q.koff;
