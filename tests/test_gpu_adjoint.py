@@ -59,15 +59,33 @@ def test_adjoint(gpu, i):
             _check(outs, ref, ("g_gout", "g_x", "g_evec", "g_phi", "g_W"), (which, list(kw)))
 
 
-def _autograd_case():
-    import torch
+def _run(degrees, i=0):
     from paper_2607_18074_amd import api
-    case = ac.case(0, (3, 0, 20, 65))
+    case = ac.case(i, degrees)
     irr_in, lmax, irr_out, K = case["sig"]
     plan, g = api.Plan(irr_in, lmax, irr_out, K), case["graph"]
     graph = api.Graph(_t(g.rowptr), _t(g.sender))
+    args, gout = [_t(v) for v in (case["x"], g.evec, g.phi, case["W"])], _t(case["gout"])
     oa = (oc.Problem(irr_in, lmax, irr_out, K), case["x"], g.evec, g.phi, case["W"], g.rowptr, g.sender)
-    return torch, api, plan, graph, case, [_t(v) for v in (case["x"], g.evec, g.phi, case["W"])], oa
+    return api, plan, graph, case, args, gout, oa
+
+
+def test_shares_of_a_receiver(gpu):
+    """Two blocks a receiver, of which the first takes a second turn for edges 128 and on, the second has none of
+    most receivers."""
+    api, plan, graph, case, args, gout, oa = _run((129, 1) + (2,) * 300 + (64, 192, 65))
+    _check(api.conv_bwd(plan, graph, *args, gout, need=(True, True, True, False)), oc.bwd(*oa, case["gout"]),
+           ("gx", "gevec", "gphi"), "bwd")
+    t = ac.cotangents(case, ("x", "evec"))
+    ref = oc.dbwd(*oa, case["gout"], t_gx=t["x"], t_gevec=t["evec"])
+    outs = api.conv_dbwd(plan, graph, *args, gout, _t(t["x"]), _t(t["evec"]), need=(False, True, True, True, False))
+    _check(outs[1:4], ref, ("g_x", "g_evec", "g_phi"), "dbwd")
+
+
+def _autograd_case():
+    import torch
+    api, plan, graph, case, args, _, oa = _run((3, 0, 20, 65))
+    return torch, api, plan, graph, case, args, oa
 
 
 @pytest.mark.parametrize("retain", [False, True])
