@@ -611,14 +611,17 @@ float* ga_partials(const Plan& p, const WsPlan& w, void* ws, int gi) {
 // within the pass's partial region; the kernel derives each group's split from ns.
 int split_mix(const Plan& p, int glo, int ghi, int r0, int n, const WsPlan& w, void* ws, const float* S,
               int64_t s_ncap, const float* W, float* out, int acc, hipStream_t s) {
+  int64_t most;   // splits of the group that has most
   auto shape = [&](int ns, int64_t& blocks, size_t& floats) {
     blocks = 0;
     floats = 0;
+    most = 1;
     for (int i = glo; i < ghi; ++i) {
       const sobek::Group& g = p.groups[i];
       const int64_t nz = cdiv(g.D, std::max<int64_t>(128, cdiv(cdiv(g.D, ns), 32) * 32));
       blocks += (int64_t)cdiv((int64_t)n * g.d, 128) * cdiv(g.C, sobek::split_bn(g.C)) * nz;
       floats += (size_t)nz * n * g.d * g.C;
+      most = std::max(most, nz);
     }
   };
   int64_t base, blocks;
@@ -627,6 +630,7 @@ int split_mix(const Plan& p, int glo, int ghi, int r0, int n, const WsPlan& w, v
   int ns = 1;
   if (n > 0 && base * 2 <= kSaTarget) ns = (int)std::min<int64_t>(kSaMaxSplit, (kSaTarget + base - 1) / base);
   for (shape(ns, blocks, floats); ns > 1 && floats > w.kfloats; shape(--ns, blocks, floats)) {}
+  if (most == 1) ns = 1;   // no reduction is long enough to be shared: straight into out
   float* K = ns > 1 ? (float*)((char*)ws + w.off_K) : nullptr;
   long long cap = s_ncap;
   LAUNCH(p.k.sp3_sa, (unsigned)blocks, 1, 1, s, S, cap, r0, n, W, (const int*)p.d_ktab, out, acc, K, ns, glo, ghi);
