@@ -91,6 +91,8 @@ void emit_split(std::ostringstream& o, const Plan& p) {
       << (int64_t)g.D * g.C << "LL;\n";
   }
   o << "}\n";
+  // Up to 64 splits of few elements: what bounds it is the latency of a thread's loads, 32 of them in flight
+  // (one at a time 33 us for 20x0e+12x1o to 36x0e+72x1o, 19 for 12x0e to 16x0e; 12 and 8 now)
   o << "extern \"C\" __global__ __launch_bounds__(256) void sobek_sp3_gared(const float* __restrict__ P, sb_i64 cap,"
        " const int* __restrict__ ktab, float* __restrict__ gW, int glo, int ghi) {\n"
        "  sb_i64 t = (sb_i64)blockIdx.x * 256 + threadIdx.x;\n";
@@ -98,7 +100,9 @@ void emit_split(std::ostringstream& o, const Plan& p) {
     const Group& g = p.groups[i];
     o << ga_group(i) << "    if (t < D * CG / 4) {\n      const int k = (int)t / (CG / 4), c = 4 * ((int)t % (CG / 4));\n"
       << "      const float* src = P + 4 * t;\n      sb_v4 v = sb_ld4(src);\n"
-      << "      for (int z = 1; z < ns; ++z) v += sb_ld4(src + (sb_i64)z * (D * CG));\n"
+      << "      for (int z = 1; z < ns; z += 32) {\n        sb_v4 u[32];\n#pragma unroll\n"
+      << "        for (int k = 0; k < 32; ++k) u[k] = sb_ld4(src + (sb_i64)min(z + k, ns - 1) * (D * CG));\n#pragma unroll\n"
+      << "        for (int k = 0; k < 32; ++k)\n          if (z + k < ns) v += u[k];\n      }\n"
       << "      *(sb_v4*)(gW + (sb_i64)ktab[" << g.ktab_off << " + k] + c) = v;\n      return;\n    }\n    t -= D * CG / 4;\n"
       << "  }\n  P += (sb_i64)min((sb_i64)" << ga_max_splits(p, g) << ", max((sb_i64)1, cap * " << g.d << " / 64)) * "
       << (int64_t)g.D * g.C << "LL;\n";
