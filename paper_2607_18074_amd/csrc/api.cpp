@@ -1001,19 +1001,20 @@ int load_receiver_route(Plan& p, hipModule_t m) {
   const char* bns[3] = {"16", "32", "64"};
   for (int b = 0; b < 3; ++b) {
     std::string sa = std::string("sobek_gemm_sa_") + bns[b], sb = std::string("sobek_gemm_sbar_") + bns[b],
-                ga = std::string("sobek_gemm_ga_") + bns[b],
-                sav = std::string(p.dtype == SOBEK_DTYPE_BF16_GEMM ? "sobek_gemm_sa_vb" : "sobek_gemm_sa_v") + bns[b],
-                gav = std::string(p.dtype == SOBEK_DTYPE_BF16_GEMM ? "sobek_gemm_ga_vb" : "sobek_gemm_ga_v") + bns[b];
+                ga = std::string("sobek_gemm_ga_") + bns[b], sav = std::string("sobek_gemm_sa_vb") + bns[b],
+                gav = std::string("sobek_gemm_ga_vb") + bns[b];
     if ((rc = get_fn(m, p.k.gemm_sa[b], sa.c_str())) || (rc = get_fn(m, p.k.gemm_sbar[b], sb.c_str())) ||
-        (rc = get_fn(m, p.k.gemm_ga[b], ga.c_str())) || (rc = get_fn(m, p.k.gemm_sa_v[b], sav.c_str())) ||
-        (rc = get_fn(m, p.k.gemm_ga_v[b], gav.c_str())))
+        (rc = get_fn(m, p.k.gemm_ga[b], ga.c_str())))
+      return rc;
+    if (p.dtype == SOBEK_DTYPE_BF16_GEMM &&   // fp32 plans that could take them have the split products
+        ((rc = get_fn(m, p.k.gemm_sa_v[b], sav.c_str())) || (rc = get_fn(m, p.k.gemm_ga_v[b], gav.c_str()))))
       return rc;
   }
   if ((rc = get_fn(m, p.k.gemm_sbar_v, "sobek_gemm_sbar_v"))) return rc;
   if (p.dtype == SOBEK_DTYPE_BF16_GEMM && (rc = get_fn(m, p.k.gemm_sa_vb128, "sobek_gemm_sa_vb128"))) return rc;
   if (p.vec4)
     for (auto& g : p.groups)
-      if (sobek::sbar_streams(p.vec4, g.C) && !p.k.gemm_sbar_c.count(g.C)) {
+      if ((sobek::sbar_fp32(p, g.C) || sobek::sbar_bf16(p, g.C)) && !p.k.gemm_sbar_c.count(g.C)) {
         std::string nm = (sobek::sbar_bf16(p, g.C) ? "sobek_gemm_sbar_cb" : "sobek_gemm_sbar_c") + std::to_string(g.C);
         hipFunction_t f = nullptr;
         if ((rc = get_fn(m, f, nm.c_str()))) return rc;

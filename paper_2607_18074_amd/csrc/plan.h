@@ -158,6 +158,10 @@ std::string generate_source(const Plan& p, bool receiver_route = true);
 // multiples of 32 up to 128 (sobek_gemm_sbar_cb<C>, 256 rows of mbar per block); other widths keep
 // the fp32 kernels (64 rows per block).
 inline bool sbar_bf16(const Plan& p, int C) { return p.dtype == 1 && sbar_streams(p.vec4, C) && C % 32 == 0 && C <= 128; }
+// the streaming fp32 form: where neither the bf16 form nor the split products (up to 128 wide) run
+inline bool sbar_fp32(const Plan& p, int C) {
+  return sbar_streams(p.vec4, C) && !sbar_bf16(p, C) && (p.mode != 0 || p.dtype != 0 || C > 128);
+}
 inline int sbar_block_rows(const Plan& p, int C) { return sbar_bf16(p, C) ? 256 : 64; }
 
 // Source of the materialized-forward baseline module (Section 2.4, eq. radial_projection_background).

@@ -33,7 +33,6 @@
 #define __builtin_amdgcn_rsqf(x) (1.0f / sqrtf(x))
 #define __builtin_amdgcn_readlane(v, l) emu_readlane((v), (l), __LINE__)
 #define __builtin_amdgcn_readfirstlane(v) (v)
-#define __builtin_amdgcn_mov_dpp(v, ctrl, rm, bm, bc) emu_mov_dpp((v), (ctrl), __LINE__)
 #define __builtin_amdgcn_ds_read_tr16_b64_v4i16(p) emu_ds_read_tr16((const void*)(uintptr_t)(p), __LINE__)
 #define SBA_SCALAR(p) ((void)0)   // scalar-register hint of the adjoint kernels
 #define __ballot(p) emu_ballot((p), __LINE__)
@@ -79,22 +78,6 @@ static inline T emu_shfl_xor_(int site, T v, int mask, int width = 64) {
   if (idx >= ((self + width) & ~(width - 1))) idx = self;
   T r;
   memcpy(&r, s + 64 * idx, sizeof(T));
-  return r;
-}
-
-// DPP move: quad permutations (0x00 - 0xff), row_ror:n (0x121 - 0x12f: lane l takes lane
-// (l - n) mod 16 of its 16-lane row), row_mirror (0x140), row_half_mirror (0x141)
-static inline int emu_mov_dpp(int v, int ctrl, int site) {
-  const unsigned char* s = emu_wave_op(&v, sizeof(int), site, nullptr);
-  const int L = emu_cur->lane;
-  int from = L;
-  if (ctrl < 0x100) from = (L & ~3) | ((ctrl >> (2 * (L & 3))) & 3);
-  else if (ctrl > 0x120 && ctrl < 0x130) from = (L & 48) | ((L - (ctrl & 15)) & 15);
-  else if (ctrl == 0x140) from = (L & 48) | (15 - (L & 15));
-  else if (ctrl == 0x141) from = (L & 56) | (7 - (L & 7));
-  else __builtin_trap();
-  int r;
-  memcpy(&r, s + 64 * from, sizeof(int));
   return r;
 }
 

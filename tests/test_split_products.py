@@ -1,5 +1,7 @@
 """The split channel products on the CPU emulation build, against the float64 oracle."""
 
+import re
+
 import pytest
 
 from oracle import conv as oc
@@ -24,3 +26,12 @@ def test_split_products(i, policy):
         assert max_rel(H.conv_fwd(plan, graph, *args, budget=budget).np(), oc.fwd(*oa)) <= sc.TOL
         for name, o in zip(("gx", "gevec", "gphi", "gW"), H.conv_bwd(plan, graph, *args, H.dev(case["gout"]), budget=budget)):
             assert max_rel(o.np(), ref[name]) <= sc.TOL, (budget, name)
+
+
+def test_only_what_runs_is_generated():
+    """The streaming adjoint-state kernel: not where the split products (fp32, up to 128 wide) or the bf16 form run."""
+    from paper_2607_18074_amd import _lib
+    sig = ("8x0e+8x1o", 1, "132x0e+4x1o+32x1e", 8)
+    for dtype, widths in (("f32", {"132"}), ("bf16_gemm", {"132", "4"})):
+        src = _lib.plan_source(*sig, "ir_mul", "none", "uvw", dtype)
+        assert set(re.findall(r"void sobek_gemm_sbar_c(\d+)\(", src)) == widths
