@@ -105,8 +105,9 @@ int sobek_version(void);
  *   dtype: SOBEK_DTYPE_F32, fp32 throughout (the paper's precision, Section 5.1);
  *          uvw plans whose multiplicities are multiples of 4 take their channel
  *          products, and some their edge adjoints, as six products of three
- *          bf16 parts of each operand (24 bits) with fp32 sums: the error is
- *          fp32's, an infinite operand gives NaN;
+ *          bf16 parts of each operand (24 bits from 2^-109 on, fewer below)
+ *          with fp32 sums: the error is fp32's, an operand above 3.396e38 or
+ *          infinite gives NaN;
  *          SOBEK_DTYPE_BF16_GEMM, a reduced-precision option for uvw plans whose
  *          multiplicities are all multiples of 4 (else SOBEK_E_UNSUPPORTED): the
  *          channel GEMMs, m = S A (Section 4.2 eq. receiver_matrix_product; the

@@ -347,9 +347,11 @@ def _c(t):
 
 # Cotangents that autograd does not have stay None (set_materialize_grads(False)): as tensors of zeros
 # they sent every double backward down the general route, with a second adjoint state for the weight
-# cotangent (W's first gradient takes no part in a loss on forces), and only the gradients that autograd
-# asks for are computed.  A force-matching step of 5,171 nodes, 150,000 edges of 64x0e+64x1o+64x2e:
-# 10.2 -> 7.3 ms.
+# cotangent (W's first gradient takes no part in a loss on forces).  Gradients of inputs that do not
+# require one are not computed; those that do get theirs, also where torch.autograd.grad names other
+# inputs (a node is told what requires a gradient, not what was asked for: the first backward of a loss
+# on forces forms W's gradient too).  A force-matching step of 5,171 nodes, 150,000 edges of
+# 64x0e+64x1o+64x2e: 10.2 -> 7.3 ms.
 
 class _TPConvBackward(torch.autograd.Function):
     @staticmethod

@@ -77,7 +77,21 @@ std::vector<AdjGroup> adjoint_groups(const Plan& p) {
 //   64x0e+64x1o+64x2e lmax 2, 6,000 receivers           30 steps   930 / 2,046   901 / 1,906
 //   128x0e+64x1o lmax 1, 20,000 receivers                8 steps   493 / 1,420   921 / 2,287
 // A receiver's first loads, Y and the outputs are a fixed cost that a few steps do not carry, and at
-// lmax 1 the coupling that is saved is small.  The line lies at the least that was level.
+// lmax 1 the coupling that is saved is small.  The line lies at the least that was level; nothing between 8
+// and 30 steps was measured.
+//
+// The choice is the plan's: the order of a kept adjoint state follows from it.  A CU holds one block of this
+// kernel and three of the per-edge one, so 513 to 768 receivers are three turns against one, and with two passes
+// against one launch few edges do not pay.  Where that shows is a double backward on a kept adjoint state (us,
+// per-edge and this; the split products make up for it where Sbar is formed in the call):
+//   edge vectors alone, 700 receivers, degree 8   64x0e+64x1o+64x2e 102 / 113, 128x0e+64x1o+64x2e 122 / 129;
+//                                                 at 400 receivers 93 / 78, 1,000 196 / 148 (the first plan)
+//   x, edge vectors, phi, 64x0e+32x1o+32x2e+32x3o degree 8: 400 receivers 223 / 240, 1,500 731 / 768; degree 28:
+//                                                 0.57 to 0.82 of the per-edge time
+// Its backward gained more each time: the two together take 0.28 to 0.98 of the time with per-edge kernels and
+// the older products (seven plans, 60 to 4,000 receivers, degree 2 to 100).  Per-edge kernels that read the
+// order of this one were 1.05 to 1.48 times slower than it there (four-byte LDS stores in their staging), and
+// the per-edge order for such graphs would cost the other cotangents up to 1.6 times.
 bool adjoint_plan(const Plan& p) {
   if (p.mode != 0 || p.K != 16 || p.lmax < 2 || p.paths.empty() || !p.vec4) return false;
   for (auto& q : p.paths)

@@ -8,7 +8,7 @@
 
 namespace sobek {
 
-// channels [U0, U0 + 64) of input irrep a; its 2 l + 1 slots start at `slot`
+// channels [U0, U0 + 16 UT) of input irrep a, UT its group's; its 2 l + 1 slots start at `slot`
 struct AdjJob {
   int a, U0, slot;
 };
@@ -18,7 +18,8 @@ struct AdjGroup {
   std::vector<AdjJob> jobs;
 };
 
-// fully connected plans with K = 16 and input multiplicities in multiples of 16
+// fully connected plans with K = 16, lmax of 2 or more, input multiplicities in multiples of 16 and at least 30
+// steps (channel tile, pair of m_y)
 bool adjoint_plan(const Plan& p);
 std::vector<AdjGroup> adjoint_groups(const Plan& p);
 // text that follows generate_split_source's and emit_sh's

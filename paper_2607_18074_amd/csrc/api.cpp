@@ -245,8 +245,9 @@ size_t partial_floats(const Plan& p, int64_t ncap, int pass = SOBEK_PASS_BWD, in
 // Split-K of the state GEMM m_g = S_g A_g: a chunk of few receivers gives few row
 // tiles against a long reduction (K times the summed input multiplicities), so the
 // reduction is split until about kSaTarget blocks run; partial tiles are summed in
-// split order by sobek_sa_reduce.  The partials of one group at a time live in a
-// region of at most kSaSplitCap floats.
+// split order by sobek_sa_reduce (one group at a time) or sobek_sp3_red (all groups of
+// a launch at once, whose number of splits falls until they fit).  The region holds
+// kSaMaxSplit partials of the widest group, at most kSaSplitCap floats.
 constexpr int kSaTarget = 512, kSaMaxSplit = 16;
 constexpr size_t kSaSplitCap = (size_t)4 << 20;
 
@@ -919,8 +920,8 @@ int adj_edge_split(const Plan& p, int nr, int64_t ne) {
 // window: a block per receiver and 64 of its edges (further 64s in the same block, or over blockIdx.y
 // when there are few receivers: as many shares as the largest in-degree has, one without edges ends at
 // once.  By the mean degree one receiver above it kept the launch for a second turn: 60 receivers of
-// 128x0e+64x1o+64x2e, backward, degree 100 88 -> 53 us, of degree 200 60 us).  sb: adjoint state, group blocks sb_ncap receivers apart, receiver ra
-// at row sb_r0.  accum, accx: add to gphi and gevec, to contrib.
+// 128x0e+64x1o+64x2e, backward, degree 100 88 -> 53 us, of degree 200 60 us).  sb: adjoint state, group
+// blocks sb_ncap receivers apart, receiver ra at row sb_r0.  accum, accx: add to gphi and gevec, to contrib.
 int run_adjoint(const Plan& p, const sobek_graph_s& G, int64_t ea, int64_t eb, int ra, int nr, const float* x,
                 const float* evec, const float* phi, const float* sb, int64_t sb_ncap, int sb_r0, bool tangent,
                 const float* evdot, const float* phidot, int flags, float* gphi, float* gevec, float* contrib,

@@ -10,8 +10,8 @@
 // product and contract the same T with Ydot, phidot and (Hessian term) phi.
 //
 // A block takes one receiver and 64 of its edges: four tiles of 16 edges, two waves a tile, one for
-// each half of a step's columns.  A step is two m_y against a group of up to eight slots (input irrep,
-// m_i) on one 16-channel tile: a wave forms one slot's Rb from the adjoint state (lane = (u, four q)),
+// each half of a step's columns.  A step is two m_y against a group of up to six slots (input irrep, m_i;
+// seven for an irrep of l = 3) on one 16-channel tile: a wave forms one slot's Rb from the adjoint state (lane = (u, four q)),
 // split into three bf16 planes in LDS (two buffers, one barrier a step), and both products read that
 // copy, the second one transposed.  The adjoint state of the next step and the sender rows of the next
 // channel tile are loaded ahead of a step's products.  The planes of phi Y are formed once per 64 edges.

@@ -4,8 +4,9 @@
 // v = h + m + l, |v - h - m - l| <= 2^-25 |v|); the six products of total order below 2^-24 (hh, hm,
 // mh, mm, hl, lh) are accumulated in fp32 by v_mfma_f32_16x16x32_bf16.  The dropped ones are below
 // 2^-25 of the product.  Measured on independent tiles: 2,230 TFLOP/s for that instruction, so 370 of
-// fp32 product, against 153 for v_mfma_f32_16x16x4_f32.  Infinite operands give NaN (their split
-// subtracts them from themselves).
+// fp32 product, against 153 for v_mfma_f32_16x16x4_f32.  That holds for magnitudes from 2^-109 (below,
+// the low part falls under bf16's smallest step, 2^-133) to 3.396e38 (above, the high part rounds to
+// infinity); an operand above that, or infinite, gives NaN (its split subtracts infinity from itself).
 //
 // Operand layout (lane l = j + 16 g): A row j and B column j supply the eight k values of slot
 // group g; D[4g + r][j] sits in accumulator register r of lane j + 16 g.
@@ -74,10 +75,10 @@ SB_DEV sbm_b4 sbm_tr4(const char* p) {
 // in flight while the matrix units work.  Operands whose reduction index is contiguous in memory are
 // stored [octet of k][row][8]; the others as loaded, [k][column], and read transposed
 // (ds_read_b64_tr_b16).  Tiles are computed transposed (D rows = output columns), so a lane ends
-// with four consecutive output columns of one row: one float4 store.  What bounds them now is S (or
-// Sbar) passing between HBM and the CUs once, at 2.8 to 3.5 TB/s; per pass over 20,000 receivers of
-// 64x0e+64x1o+64x1e+64x2e at K = 16 (5.2 GB of state), fp32 matrix instructions before and now:
-// m = S A 2.80 -> 1.86 ms, Sbar 3.23 -> 1.51 ms, A_bar 2.86 -> 1.67 ms.  Loads are never conditional
+// with four consecutive output columns of one row: one float4 store.  S (or Sbar) passes between HBM
+// and the CUs once, at 2.8 to 3.5 TB/s of the 4.7 of a copy (what holds the rest was not measured); per
+// pass over 20,000 receivers of 64x0e+64x1o+64x1e+64x2e at K = 16 (5.2 GB of state), fp32 matrix
+// instructions before and now: m = S A 2.80 -> 1.86 ms, Sbar 3.23 -> 1.51 ms, A_bar 2.86 -> 1.67 ms.  Loads are never conditional
 // (addresses are clamped into the operand; what lies past the reduction's end is zeroed on its way to
 // LDS, in one of the two operands; rows and columns past the edge are not stored).
 
@@ -293,10 +294,12 @@ SB_DEV void sp3_ga(char* lds, const float* __restrict__ S, const float* __restri
 
 // 128 rows of mbar against the k tiles [t0, t1) of 64 columns.  A wave keeps the planes of its 32 rows
 // in registers (they pass through LDS once, 32 w at a time); A's rows of the next tile are loaded
-// while the current one is multiplied.  CG up to 128.
+// while the current one is multiplied.  CG up to 128; the planes of 128 columns do not all fit the
+// registers (65 to 195 of a lane's are spilled; with that, 6,000 receivers of 128x0e+128x1o+128x2e+64x3o
+// at K = 16 3.67 -> 3.06 ms, of 128x0e+64x1o+64x2e 0.64 -> 0.44).
 #define SP3_AOC (64 * 16 + 64)             // bytes between octets of a 64-row block
 constexpr int sp3_lds_sbar(int CG) {
-  const int a = 3 * (CG + 31) / 32 * 4 * SP3_AOC;
+  const int a = 3 * ((CG + 31) / 32) * 4 * SP3_AOC;
   return a > 3 * SP3_KPL ? a : 3 * SP3_KPL;
 }
 template <int D, int DG, int CG, int OFF>
